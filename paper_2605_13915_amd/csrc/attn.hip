@@ -19,6 +19,8 @@
 // long as both operands agree; for P.V the k slot (kg, 4*jq+tt) stands for token
 // 16*tt + 4*kg + jq of the tile, which lets P travel as one packed dword per lane and lets V
 // be brought into "token-contiguous" order by 4x4 byte transposes (v_perm_b32) in registers.
+#include <algorithm>
+
 #include "attn_kernel.hpp"
 
 namespace msd {
@@ -34,44 +36,76 @@ static int launch_attn_for_group(const AttnParams& p, dim3 grid, hipStream_t str
 // (times s_V per channel in per-channel mode; Alg. 3 last two steps).  A second launch: a
 // release/acquire handshake inside the main kernel costs far more than the launch (every
 // workgroup's agent-scope release fence forces an L2 write-back under the KV stream).
+//
+// One workgroup per query row.  Latency is all it is made of, so no load depends on another: the weights of the
+// parts are formed by either wave (a lane per part) while four groups of 32 threads request every fourth part with
+// 16-byte loads (four in flight); the groups' sums meet in LDS.
+template <bool BAL>
 __global__ __launch_bounds__(kD) void attn_combine_kernel(AttnParams p, int per_channel) {
+  __shared__ __attribute__((aligned(16))) float s_o[4][kD];
   const int row = blockIdx.x;  // b*Hq + hq
   const int b = row / p.Hq, hq = row % p.Hq;
   const int hk = hq / p.G, h = hq % p.G;
-  const int c = threadIdx.x;
-  const int64_t base = ((int64_t)(b * p.Hkv + hk) * p.nsplit) * p.G + h;
-  float ms = -INFINITY;
-  for (int s = 0; s < p.nsplit; ++s) ms = fmaxf(ms, p.part_m[base + (int64_t)s * p.G]);
-  float o = 0.f, l = 0.f;
-  for (int s = 0; s < p.nsplit; ++s) {
-    const int64_t pr = base + (int64_t)s * p.G;
-    const float mv = p.part_m[pr];
-    const float wgt = (mv == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mv - ms);
-    o += p.part_o[pr * kD + c] * wgt;
-    l += p.part_l[pr] * wgt;
+  const int tid = threadIdx.x, lane = tid & 63;
+  int n = p.nsplit;
+  int64_t first = ((int64_t)b * p.Hkv + hk) * p.nsplit;  // the splits of the row: consecutive slots
+  if constexpr (BAL) {
+    first = (int64_t)hk * (p.B * p.nsplit) + p.part_of[2 * b];
+    n = p.part_of[2 * b + 1];
   }
-  float v = l > 0.f ? __fdiv_rn(o, l) : 0.f;
-  if (per_channel) v *= p.v_scale[hk * kD + c];
+  const int64_t base = first * p.G + h;
+  const bool have = lane < n;
+  const float m = have ? p.part_m[base + (int64_t)lane * p.G] : -INFINITY;
+  const float lp = have ? p.part_l[base + (int64_t)lane * p.G] : 0.f;
+  const int c4 = (tid & 31) * 4, grp = tid >> 5;
+  v4f v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)  // the first sixteen parts: requested before the weights are known
+    v[u] = *reinterpret_cast<const v4f*>(p.part_o + (base + (int64_t)min(grp + 4 * u, n - 1) * p.G) * kD + c4);
+  const float ms = wave_max(m);
+  const float wl = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - ms);  // the weight of part `lane`
+  const float l = wave_sum(lp * wl);
+  v4f o = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < n; s0 += 16) {
+    if (s0 > 0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        v[u] = *reinterpret_cast<const v4f*>(p.part_o + (base + (int64_t)min(s0 + grp + 4 * u, n - 1) * p.G) * kD + c4);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int s = s0 + grp + 4 * u;
+      const float w = __shfl(wl, s & 63);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] += s < n ? v[u][e] * w : 0.f;
+    }
+  }
+  *reinterpret_cast<v4f*>(&s_o[grp][c4]) = o;
+  __syncthreads();
+  const int c = tid;
+  const float sum = (s_o[0][c] + s_o[1][c]) + (s_o[2][c] + s_o[3][c]);
+  float r = l > 0.f ? __fdiv_rn(sum, l) : 0.f;
+  if (per_channel) r *= p.v_scale[hk * kD + c];
   if (p.out_bf16)
-    reinterpret_cast<uint16_t*>(p.out)[(int64_t)row * kD + c] = f32_to_bf16_bits(v);
+    reinterpret_cast<uint16_t*>(p.out)[(int64_t)row * kD + c] = f32_to_bf16_bits(r);
   else
-    reinterpret_cast<float*>(p.out)[(int64_t)row * kD + c] = v;
+    reinterpret_cast<float*>(p.out)[(int64_t)row * kD + c] = r;
 }
 
 size_t attn_workspace_bytes(int B, int Hq, int Hkv, int d, int64_t L) {
   (void)d;
-  const int ns = attn_plan_nsplit(B, Hkv, L);
+  const int ns = std::max(attn_plan_nsplit(B, Hkv, Hkv > 0 ? Hq / Hkv : 1, L), attn_dequant_plan_nsplit(B, Hkv, L));
   const size_t rows = (size_t)B * Hq * ns;
-  return align_up(rows * kD * 4, 256) + 2 * align_up(rows * 4, 256);
+  return align_up(rows * kD * 4, 256) + 2 * align_up(rows * 4, 256) + align_up((size_t)B * 8, 256);
 }
 
-void attn_fill_params(const AttnArgs& a, AttnParams& p) {
+void attn_fill_params(const AttnArgs& a, int nsplit, AttnParams& p) {
   p.q = a.q; p.K = a.K; p.V = a.V;
   p.k_scale = a.k_scale; p.v_scale = a.v_scale;
   p.kv_len = a.kv_len;
   p.B = a.B; p.Hq = a.Hq; p.Hkv = a.Hkv; p.G = a.Hq / a.Hkv;
   p.L = a.L;
-  p.nsplit = attn_plan_nsplit(a.B, a.Hkv, a.L);
+  p.nsplit = nsplit;
   int64_t tps = cdiv(a.L > 0 ? a.L : 1, p.nsplit);
   tps = cdiv(tps, kAttnWaves * kTile) * (kAttnWaves * kTile);
   p.tokens_per_split = tps;
@@ -80,19 +114,24 @@ void attn_fill_params(const AttnArgs& a, AttnParams& p) {
   p.part_o = (float*)ws;
   p.part_m = (float*)(ws + align_up(rows * kD * 4, 256));
   p.part_l = (float*)(ws + align_up(rows * kD * 4, 256) + align_up(rows * 4, 256));
+  p.part_of = (int32_t*)(ws + align_up(rows * kD * 4, 256) + 2 * align_up(rows * 4, 256));
   p.out = a.out;
   p.out_bf16 = a.out_bf16;
 }
 
 int launch_attn_combine(const AttnParams& p, int per_channel, hipStream_t stream) {
-  hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)(p.B * p.Hq)), dim3(kD), 0, stream, p, per_channel);
+  const dim3 grid((unsigned)(p.B * p.Hq));
+  if (p.balanced)
+    hipLaunchKernelGGL((attn_combine_kernel<true>), grid, dim3(kD), 0, stream, p, per_channel);
+  else
+    hipLaunchKernelGGL((attn_combine_kernel<false>), grid, dim3(kD), 0, stream, p, per_channel);
   MSD_LAUNCH_CHECK();
   return MSD_OK;
 }
 
 int launch_attn_decode(const AttnArgs& a, hipStream_t stream) {
   AttnParams p{};
-  attn_fill_params(a, p);
+  attn_fill_params(a, attn_plan_nsplit(a.B, a.Hkv, a.Hq / a.Hkv, a.L), p);
   if (a.taps) {
     p.tap_q1 = (int8_t*)a.taps->q1;
     p.tap_q2 = (int8_t*)a.taps->q2;
@@ -105,6 +144,7 @@ int launch_attn_decode(const AttnArgs& a, hipStream_t stream) {
     p.tap_p2 = (int8_t*)a.taps->p2;
     if (!(p.tap_p1 && p.tap_p2)) p.tap_p1 = p.tap_p2 = nullptr;
   }
+  p.balanced = a.kv_len != nullptr && p.nsplit > 1 && a.B <= kBalancedMaxB && a.B > 1 && !a.lowprec;
   const dim3 grid((unsigned)((int64_t)a.B * a.Hkv * p.nsplit));
   const bool per_token = a.scale_mode == MSD_PER_TOKEN;
   int rc;

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_dequant_kernel(AttnParam
 
 int launch_attn_dequant(const AttnArgs& a, hipStream_t stream) {
   AttnParams p{};
-  attn_fill_params(a, p);
+  attn_fill_params(a, attn_dequant_plan_nsplit(a.B, a.Hkv, a.L), p);
   const dim3 grid((unsigned)((int64_t)a.B * a.Hkv * p.nsplit));
   const bool per_token = a.scale_mode == MSD_PER_TOKEN;
   if (p.G <= kCmpHeads) {

@@ -31,7 +31,10 @@ namespace msd {
 // same for small probabilities, a relative 2^-11 for the largest ones.
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
-template <int HPL, bool PER_TOKEN, bool MULTI, int NF, bool LOWP = false>
+//
+// BAL: the splits follow the lengths of a ragged batch (balanced_splits); an instance of its own, since the other
+// calls would pay for the longer prologue (0.3 us of 8).
+template <int HPL, bool PER_TOKEN, bool MULTI, int NF, bool LOWP = false, bool BAL = false>
 __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_kernel(AttnParams p, int nh_total) {
   constexpr int HF = 4 * HPL;  // heads per fragment
   constexpr int NH = HF * NF;  // head slots of one pass
@@ -47,13 +50,29 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_kernel(AttnParams
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 15, g = lane >> 4;  // g: lane group = head group in D layouts; kg for operands
-  const int bk = blockIdx.x / p.nsplit, split = blockIdx.x % p.nsplit;
-  const int b = bk / p.Hkv, hk = bk % p.Hkv;
   const int G = p.G;
-  int64_t len = p.kv_len ? (int64_t)p.kv_len[b] : p.L;
-  len = max((int64_t)0, min(len, p.L));
-  const int64_t t_begin = (int64_t)split * p.tokens_per_split;
-  const int64_t t_end = min(len, t_begin + p.tokens_per_split);
+  int b, hk, split;
+  int64_t t_begin, t_end;
+  if constexpr (BAL) {
+    const int slots = p.B * p.nsplit, slot = blockIdx.x % slots;
+    hk = blockIdx.x / slots;
+    const BalancedSplits plan = balanced_splits(p.kv_len, p.L, p.B, slots, kTile, lane);
+    if (!balanced_slot(plan, p.B, slot, kTile, lane, b, split, t_begin, t_end)) return;
+    if (hk == 0 && split == 0 && tid == 0) {
+      p.part_of[2 * b] = slot;
+      p.part_of[2 * b + 1] = __builtin_amdgcn_readlane(plan.n, b);
+    }
+  } else {
+    const int pair = blockIdx.x / p.nsplit;
+    split = blockIdx.x % p.nsplit;
+    b = pair / p.Hkv;
+    hk = pair % p.Hkv;
+    int64_t len = p.kv_len ? (int64_t)p.kv_len[b] : p.L;
+    len = max((int64_t)0, min(len, p.L));
+    t_begin = (int64_t)split * p.tokens_per_split;
+    t_end = min(len, t_begin + p.tokens_per_split);
+  }
+  const int bk = b * p.Hkv + hk;
   const int64_t kv_base = (int64_t)bk * p.L;  // token index base of this (b, kv head)
   const int8_t* Kb = p.K + kv_base * kD;
   const int8_t* Vb = p.V + kv_base * kD;
@@ -369,7 +388,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_kernel(AttnParams
       else
         reinterpret_cast<float*>(p.out)[orow * kD + c] = v;
     } else {
-      const int64_t pr = ((int64_t)bk * p.nsplit + split) * G + h;
+      const int64_t pr = (int64_t)blockIdx.x * G + h;
       p.part_o[pr * kD + c] = o;
       if (c == 0) {
         p.part_m[pr] = ms;
@@ -381,21 +400,28 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_kernel(AttnParams
   }
 }
 
-template <int HPL, bool PER_TOKEN, bool MULTI, int NF, bool LOWP = false>
-int launch_attn_variant(const AttnParams& p, dim3 grid, hipStream_t stream) {
+template <int HPL, bool PER_TOKEN, bool MULTI, int NF, bool LOWP, bool BAL>
+int launch_attn_instance(const AttnParams& p, dim3 grid, hipStream_t stream) {
   constexpr int HF = 4 * HPL, NH = HF * NF;
   const int nh_total = (int)cdiv(p.G, NH) * NH;
   const size_t lds = (size_t)kAttnWaves * NH * kD * 4 + kAttnWaves * 2 * HF * 64 + 2 * kAttnWaves * NH * 4 +
                      (size_t)nh_total * 4 + (size_t)2 * nh_total * kD;
   static size_t attr_bytes = 64 * 1024;
   if (lds > attr_bytes) {
-    MSD_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_decode_kernel<HPL, PER_TOKEN, MULTI, NF, LOWP>),
+    MSD_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_decode_kernel<HPL, PER_TOKEN, MULTI, NF, LOWP, BAL>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     attr_bytes = lds;
   }
-  hipLaunchKernelGGL((attn_decode_kernel<HPL, PER_TOKEN, MULTI, NF, LOWP>), grid, dim3(kAttnWaves * 64), lds, stream, p, nh_total);
+  hipLaunchKernelGGL((attn_decode_kernel<HPL, PER_TOKEN, MULTI, NF, LOWP, BAL>), grid, dim3(kAttnWaves * 64), lds, stream, p, nh_total);
   MSD_LAUNCH_CHECK();
   return MSD_OK;
+}
+
+template <int HPL, bool PER_TOKEN, bool MULTI, int NF, bool LOWP = false>
+int launch_attn_variant(const AttnParams& p, dim3 grid, hipStream_t stream) {
+  if constexpr (!LOWP)
+    if (p.balanced) return launch_attn_instance<HPL, PER_TOKEN, MULTI, NF, LOWP, true>(p, grid, stream);
+  return launch_attn_instance<HPL, PER_TOKEN, MULTI, NF, LOWP, false>(p, grid, stream);
 }
 
 }  // namespace msd

@@ -59,6 +59,7 @@ struct MlaParams {
   int nsplit;  // workgroups along the KV length
   int nparts;  // partial results per (batch, head): one per KV split
   int64_t tokens_per_split;
+  int balanced;         // the splits follow the lengths (balanced_splits)
   float sm_scale_log2;  // score scale times log2(e)
   int8_t* qc1;          // [B][Hq][576] query codes of both components and alpha_Q [B][Hq] (workspace; only
   int8_t* qc2;          // used by the layout that leaves the query decomposition to its own kernel)
@@ -66,6 +67,7 @@ struct MlaParams {
   float* part_o;        // [B][nparts][Hq][512]
   float* part_m;        // [B][nparts][Hq]
   float* part_l;
+  int32_t* part_of;     // balanced splits: first slot and slot count of every entry, [B][2]
   void* out;
   int out_bf16;
   int8_t* tap_q1;
@@ -151,7 +153,8 @@ __global__ __launch_bounds__(256) void mla_q_decompose_kernel(MlaParams p, int p
   }
 }
 
-template <bool PER_TOKEN, int MG, int NW, int HGW, int CH>
+// BAL: the splits follow the lengths of a ragged batch (balanced_splits).
+template <bool PER_TOKEN, int MG, int NW, int HGW, int CH, bool BAL>
 __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   using Cfg = MlaCfg<MG, NW, HGW, CH>;
   constexpr int TS = Cfg::kTS, WS = Cfg::kWS, NSL = Cfg::kSlabs, NLD = Cfg::kLoads;
@@ -165,14 +168,27 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 15, g = lane >> 4;
   const int ts = wave / WS, hg = (wave / CH) % HGW, ch = wave % CH;
-  const int b = blockIdx.x / p.nsplit, split = blockIdx.x % p.nsplit;
   const int Hq = p.Hq;
   const int hb = blockIdx.y * Cfg::kHeadsWg;  // first head of this workgroup
   const int hw = hb + Cfg::kHeadsWave * hg;    // first head of this wave
-  int64_t len = p.kv_len ? (int64_t)p.kv_len[b] : p.L;
-  len = max((int64_t)0, min(len, p.L));
-  const int64_t t_begin = (int64_t)split * p.tokens_per_split;
-  const int64_t t_end = min(len, t_begin + p.tokens_per_split);
+  int b, split;
+  int64_t t_begin, t_end;
+  if constexpr (BAL) {
+    const int slots = p.B * p.nsplit;
+    const BalancedSplits plan = balanced_splits(p.kv_len, p.L, p.B, slots, TS * kTile, lane);
+    if (!balanced_slot(plan, p.B, blockIdx.x, TS * kTile, lane, b, split, t_begin, t_end)) return;
+    if (blockIdx.y == 0 && split == 0 && tid == 0) {
+      p.part_of[2 * b] = blockIdx.x;
+      p.part_of[2 * b + 1] = __builtin_amdgcn_readlane(plan.n, b);
+    }
+  } else {
+    b = blockIdx.x / p.nsplit;
+    split = blockIdx.x % p.nsplit;
+    int64_t len = p.kv_len ? (int64_t)p.kv_len[b] : p.L;
+    len = max((int64_t)0, min(len, p.L));
+    t_begin = (int64_t)split * p.tokens_per_split;
+    t_end = min(len, t_begin + p.tokens_per_split);
+  }
   const int64_t last = max(t_end - 1, (int64_t)0);
   const int8_t* Cb = p.C + (int64_t)b * p.L * p.ld;
   const float* sc_tok = p.scale + (int64_t)b * p.L;  // per-token mode only
@@ -576,7 +592,6 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   }
   // ---- the partial (m, l, O) of this wave's heads and value channels: one per KV split
   static_assert(TS <= 2, "token streams are merged pairwise above");
-  const int part = split;
 #pragma unroll
   for (int mg = 0; mg < MG; ++mg)
 #pragma unroll
@@ -600,7 +615,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
               reinterpret_cast<float*>(p.out)[orow * kLatV + col] = v;
           }
       } else {
-        const int64_t pr = ((int64_t)b * p.nparts + part) * Hq + head;
+        const int64_t pr = (int64_t)blockIdx.x * Hq + head;  // nparts == nsplit
 #pragma unroll
         for (int sl = 0; sl < NSL; ++sl)
 #pragma unroll
@@ -617,16 +632,22 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
 // Merge the partials (Alg. 3 last two steps; see attn.hip for why this is a launch of its own).  One
 // workgroup per (batch, head): the weights of the parts are formed once in LDS, then every thread sums
 // four channels over the parts with independent 16-byte loads.
-constexpr int kMlaMaxParts = 64;
+template <bool BAL>
 __global__ __launch_bounds__(128) void attn_mla_combine_kernel(MlaParams p, int per_channel) {
-  __shared__ float s_w[kMlaMaxParts];
+  __shared__ float s_w[kMaxParts];
   __shared__ float s_linv;
   const int row = blockIdx.x;  // b*Hq + h
   const int b = row / p.Hq, h = row % p.Hq;
-  const int64_t base = (int64_t)b * p.nparts * p.Hq + h;
+  int n = p.nparts;
+  int64_t first = (int64_t)b * p.nparts;
+  if constexpr (BAL) {
+    first = p.part_of[2 * b];
+    n = p.part_of[2 * b + 1];
+  }
+  const int64_t base = first * p.Hq + h;
   if (threadIdx.x < 64) {
     const int s = threadIdx.x;
-    const bool have = s < p.nparts;
+    const bool have = s < n;
     const float m = have ? p.part_m[base + (int64_t)s * p.Hq] : -INFINITY;
     const float lp = have ? p.part_l[base + (int64_t)s * p.Hq] : 0.f;
     const float ms = wave_max(m);
@@ -641,7 +662,7 @@ __global__ __launch_bounds__(128) void attn_mla_combine_kernel(MlaParams p, int 
   const int c = 4 * threadIdx.x;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-  for (int s = 0; s < p.nparts; ++s) {
+  for (int s = 0; s < n; ++s) {
     const float w = s_w[s];
     const float4 v = *reinterpret_cast<const float4*>(p.part_o + (base + (int64_t)s * p.Hq) * kLatV + c);
     o.x += v.x * w; o.y += v.y * w; o.z += v.z * w; o.w += v.w * w;
@@ -658,9 +679,9 @@ __global__ __launch_bounds__(128) void attn_mla_combine_kernel(MlaParams p, int 
   }
 }
 
-// Wave layout by head count, KV splits (about kMlaTargetWgs workgroups: one per CU holds the registers
-// and LDS of this kernel; every token stream of a split gets at least two tiles) and partial count.
-constexpr int kMlaTargetWgs = 256;
+// Wave layout by head count, KV splits (plan_nsplit; one workgroup per CU holds the registers and LDS of this
+// kernel) and partial count.
+constexpr int kMlaTargetWgs = 256;  // of the comparison kernel
 struct MlaPlan {
   int layout;  // 0: up to 16 heads, 1: up to 32, 2: 64 per workgroup
   int ts, heads_wg, head_blocks, nsplit, nparts;
@@ -677,37 +698,39 @@ MlaPlan mla_plan(int B, int Hq, int64_t L) {
   pl.heads_wg = pl.layout == 0 ? MlaCfg<MSD_MLA_LAYOUT_0>::kHeadsWg
                                : (pl.layout == 1 ? MlaCfg<MSD_MLA_LAYOUT_1>::kHeadsWg : MlaCfg<MSD_MLA_LAYOUT_2>::kHeadsWg);
   pl.head_blocks = (Hq + pl.heads_wg - 1) / pl.heads_wg;
-  int64_t ns = cdiv((int64_t)kMlaTargetWgs, (int64_t)B * pl.head_blocks);
-  const int64_t max_by_len = max((int64_t)1, L / (2 * pl.ts * kTile));
-  ns = max((int64_t)1, min(min(ns, max_by_len), (int64_t)kMlaMaxParts));
-  pl.nsplit = (int)ns;
+  // one workgroup per CU; a round (one tile of every token stream) costs about what it costs to multiply it, more
+  // for more heads per wave group; the merge reads 2 KB per head and part.  Against 256 workgroups
+  // and two rounds per split whatever the batch (us): 8 x 1000 tokens, 16 heads 21.8 -> 16.3; 6 x 15147, 128 heads 94 ->
+  // 60; 33 x 30561 ragged, 128 heads 816 -> 393; 32 x 4096, 128 heads unchanged
+  const SplitCost cost = {pl.ts * kTile, pl.layout == 2 ? 4000 : 2700, 1, 10000, 0, 4000, 100 + (int64_t)B * Hq * 2048 / 4000};
+  pl.nsplit = plan_nsplit((int64_t)B * pl.head_blocks, L, cost);
   pl.nparts = pl.nsplit;  // the token streams of a workgroup merge inside it
-  int64_t tps = cdiv(L > 0 ? L : 1, ns);
+  const int64_t tps = cdiv(L > 0 ? L : 1, pl.nsplit);
   pl.tokens_per_split = cdiv(tps, (int64_t)pl.ts * kTile) * (pl.ts * kTile);
   return pl;
 }
 
-template <bool PER_TOKEN, int MG, int NW, int HGW, int CH>
+template <bool PER_TOKEN, int MG, int NW, int HGW, int CH, bool BAL>
 int launch_mla_layout(const MlaParams& p, const MlaPlan& pl, hipStream_t stream) {
   constexpr size_t lds = MlaCfg<MG, NW, HGW, CH>::kLds;
   static bool attr_set = false;
   if (!attr_set) {
-    MSD_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mla_kernel<PER_TOKEN, MG, NW, HGW, CH>),
+    MSD_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mla_kernel<PER_TOKEN, MG, NW, HGW, CH, BAL>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     attr_set = true;
   }
   const dim3 grid((unsigned)((int64_t)p.B * p.nsplit), (unsigned)pl.head_blocks);
-  hipLaunchKernelGGL((attn_mla_kernel<PER_TOKEN, MG, NW, HGW, CH>), grid, dim3(NW * 64), lds, stream, p);
+  hipLaunchKernelGGL((attn_mla_kernel<PER_TOKEN, MG, NW, HGW, CH, BAL>), grid, dim3(NW * 64), lds, stream, p);
   MSD_LAUNCH_CHECK();
   return MSD_OK;
 }
 
-template <bool PER_TOKEN>
+template <bool PER_TOKEN, bool BAL>
 int launch_mla_mode(const MlaParams& p, const MlaPlan& pl, hipStream_t stream) {
   switch (pl.layout) {
-    case 0: return launch_mla_layout<PER_TOKEN, MSD_MLA_LAYOUT_0>(p, pl, stream);
-    case 1: return launch_mla_layout<PER_TOKEN, MSD_MLA_LAYOUT_1>(p, pl, stream);
-    default: return launch_mla_layout<PER_TOKEN, MSD_MLA_LAYOUT_2>(p, pl, stream);
+    case 0: return launch_mla_layout<PER_TOKEN, MSD_MLA_LAYOUT_0, BAL>(p, pl, stream);
+    case 1: return launch_mla_layout<PER_TOKEN, MSD_MLA_LAYOUT_1, BAL>(p, pl, stream);
+    default: return launch_mla_layout<PER_TOKEN, MSD_MLA_LAYOUT_2, BAL>(p, pl, stream);
   }
 }
 
@@ -978,7 +1001,8 @@ static size_t mla_partial_bytes(size_t rows) { return align_up(rows * kLatV * 4,
 size_t attn_mla_workspace_bytes(int B, int Hq, int64_t L) {
   const size_t rows = (size_t)B * Hq * mla_plan(B, Hq, L).nparts;
   const size_t qrows = (size_t)B * Hq;
-  const size_t msd = mla_partial_bytes(rows) + 2 * align_up(qrows * kLatK, 256) + align_up(qrows * 4, 256);
+  const size_t msd = mla_partial_bytes(rows) + 2 * align_up(qrows * kLatK, 256) + align_up(qrows * 4, 256) +
+                     align_up((size_t)B * 8, 256);
   // the comparison kernel shares the entry point's workspace contract (it never needs more in practice)
   return std::max(msd, mla_partial_bytes((size_t)B * Hq * mla_cmp_plan(B, Hq, L).nsplit));
 }
@@ -1015,7 +1039,7 @@ int launch_attn_mla_dequant(const AttnMlaArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL((attn_mla_dequant_kernel<false>), grid, dim3(kCmpWaves * 64), kCmpLds, stream, p);
   MSD_LAUNCH_CHECK();
   if (p.nparts > 1) {
-    hipLaunchKernelGGL(attn_mla_combine_kernel, dim3((unsigned)(a.B * a.Hq)), dim3(128), 0, stream, p,
+    hipLaunchKernelGGL((p.balanced ? attn_mla_combine_kernel<true> : attn_mla_combine_kernel<false>), dim3((unsigned)(a.B * a.Hq)), dim3(128), 0, stream, p,
                        per_token ? 0 : 1);
     MSD_LAUNCH_CHECK();
   }
@@ -1030,6 +1054,7 @@ int launch_attn_mla(const AttnMlaArgs& a, hipStream_t stream) {
   p.nsplit = pl.nsplit;
   p.nparts = pl.nparts;
   p.tokens_per_split = pl.tokens_per_split;
+  p.balanced = a.kv_len != nullptr && pl.nsplit > 1 && a.B <= kBalancedMaxB && a.B > 1;
   p.sm_scale_log2 = a.sm_scale * kLog2e;
   const size_t rows = (size_t)a.B * a.Hq * pl.nparts;
   char* ws = (char*)a.workspace;
@@ -1041,6 +1066,7 @@ int launch_attn_mla(const AttnMlaArgs& a, hipStream_t stream) {
   p.qc1 = (int8_t*)qws;
   p.qc2 = (int8_t*)(qws + align_up(qrows * kLatK, 256));
   p.qalpha = (float*)(qws + 2 * align_up(qrows * kLatK, 256));
+  p.part_of = (int32_t*)(qws + 2 * align_up(qrows * kLatK, 256) + align_up(qrows * 4, 256));
   p.out = a.out;
   p.out_bf16 = a.out_bf16;
   if (a.taps) {
@@ -1058,10 +1084,11 @@ int launch_attn_mla(const AttnMlaArgs& a, hipStream_t stream) {
                        per_token ? 0 : 1);
     MSD_LAUNCH_CHECK();
   }
-  const int rc = per_token ? launch_mla_mode<true>(p, pl, stream) : launch_mla_mode<false>(p, pl, stream);
+  const int rc = p.balanced ? (per_token ? launch_mla_mode<true, true>(p, pl, stream) : launch_mla_mode<false, true>(p, pl, stream))
+                            : (per_token ? launch_mla_mode<true, false>(p, pl, stream) : launch_mla_mode<false, false>(p, pl, stream));
   if (rc != MSD_OK) return rc;
   if (p.nparts > 1) {
-    hipLaunchKernelGGL(attn_mla_combine_kernel, dim3((unsigned)(a.B * a.Hq)), dim3(128), 0, stream, p,
+    hipLaunchKernelGGL((p.balanced ? attn_mla_combine_kernel<true> : attn_mla_combine_kernel<false>), dim3((unsigned)(a.B * a.Hq)), dim3(128), 0, stream, p,
                        per_token ? 0 : 1);
     MSD_LAUNCH_CHECK();
   }

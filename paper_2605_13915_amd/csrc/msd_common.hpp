@@ -78,6 +78,17 @@ __device__ __forceinline__ float wave_max(float v) {
   return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
 
+// Sum over the 64 lanes of a full wave, returned in every lane (the same steps).
+__device__ __forceinline__ float wave_sum(float v) {
+  v += row16_ror<8>(v);
+  v += row16_ror<4>(v);
+  v += row16_ror<2>(v);
+  v += row16_ror<1>(v);
+  const int b = __float_as_int(v);
+  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) + __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) + __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+}
+
 // One step of the two-pass INT8 decomposition (paper Sec. 3.2): given alpha, beta (already
 // rounded fp32 quotients) produce the two codes of x.  Correctly rounded division,
 // round-half-to-even, fused residual.
