@@ -86,19 +86,20 @@ struct MlaCfg {
   static constexpr int kLoads = (36 + kLanesRow - 1) / kLanesRow;  // 16-byte pieces per lane per tile
   static constexpr int kHeadsWave = 8 * MG;
   static constexpr int kHeadsWg = kHeadsWave * HGW;
-  // tiles[streams][2] | sP[waves][MG frag][2 comp][8 heads][16] u32 | sAlpha[heads] |
-  // sQ[HGW][MG][9 chunks][64 lanes][16 B]: the A fragments (over the tiles when they end up in registers)
-  static constexpr bool kQReg = HGW <= 2;  // A fragments in registers: their LDS image is only a staging area
-  static constexpr size_t kLds = (size_t)2 * kTS * kTileBytes + NW * MG * 2 * 8 * 64 + kHeadsWg * 4 +
-                                 (kQReg ? 0 : HGW * MG * 9 * 1024);
+  // tiles[streams][kBufs] | sP[waves][MG frag][2 comp][8 heads][16] u32 | sAlpha[heads]; the A fragments
+  // [HGW][MG][9 chunks][64 lanes][16 B] are put together over the tiles and then live in registers
+  static constexpr int kBufs = kTS == 1 ? 3 : 2;  // tile buffers per stream
+  static constexpr size_t kSmall = (size_t)kBufs * kTS * kTileBytes;  // offset of sP
+  static constexpr size_t kLds = kSmall + NW * MG * 2 * 8 * 64 + kHeadsWg * 4;
   static_assert(kTS * kWS == NW && kTS >= 1, "wave layout");
+  static_assert((size_t)HGW * MG * 9 * 1024 <= kSmall, "staging area");
   static_assert(kLds <= 160 * 1024, "LDS");
 };
 
 // Alg. 3 steps 1-2 for the query rows as a kernel of its own, one wave per (batch, head) row; the per-channel
 // key scale, if any, is absorbed into the row first.  Used with the 64-heads-per-workgroup layout, where the
 // prologue version would spend more vector-ALU time per CU (8 heads per wave, every KV split again) than this
-// launch costs; codes and alpha_Q go to the workspace, where the main kernel picks up its A fragments.
+// launch costs (measured 78 against 76.5 us at 32 x 4096 tokens, 128 heads; 29 against 23 at one entry); codes and alpha_Q go to the workspace, where the main kernel picks up its A fragments.
 __global__ __launch_bounds__(256) void mla_q_decompose_kernel(MlaParams p, int per_channel) {
   const int lane = threadIdx.x & 63;
   const int64_t qrow = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -121,8 +122,8 @@ __global__ __launch_bounds__(256) void mla_q_decompose_kernel(MlaParams p, int p
   mx = wave_max(mx);
   const float alpha = mx > 0.f ? __fdiv_rn(mx, 127.0f) : 0.f;
   const float beta = __fdiv_rn(alpha, 254.0f);
-  // reciprocal route with exact-division fallback (same codes); needs a normal beta
-  const bool fast = beta >= 1.17549435e-38f;
+  // without a division per element (same codes) unless the row needs them
+  const bool fast = mx > 0.f && !needs_divisions(alpha, beta);
   const float ra = fast ? __fdiv_rn(1.0f, alpha) : 0.f, rb = fast ? __fdiv_rn(1.0f, beta) : 0.f;
 #pragma unroll
   for (int bi = 0; bi < 3; ++bi) {
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(256) void mla_q_decompose_kernel(MlaParams p, int p
     for (int e = 0; e < 4; ++e) {
       int c1 = 0, c2 = 0;
       if (fast)
-        int8_codes_fast(x[bi][e], alpha, ra, beta, rb, c1, c2);
+        int8_codes_by_reciprocal(x[bi][e], alpha, ra, beta, rb, c1, c2);
       else if (mx > 0.f)
         int8_codes(x[bi][e], alpha, beta, c1, c2);
       w1 |= ((uint32_t)c1 & 0xFFu) << (8 * e);
@@ -160,10 +161,10 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   constexpr int TS = Cfg::kTS, WS = Cfg::kWS, NSL = Cfg::kSlabs, NLD = Cfg::kLoads;
   extern __shared__ __attribute__((aligned(16))) uint8_t s_mla[];
   uint8_t* sTiles = s_mla;
-  constexpr bool QREG = Cfg::kQReg;
-  uint32_t(*sP)[MG][2][8][16] = reinterpret_cast<uint32_t(*)[MG][2][8][16]>(s_mla + 2 * TS * kTileBytes);
-  float* sAlpha = reinterpret_cast<float*>(s_mla + 2 * TS * kTileBytes + NW * MG * 2 * 8 * 64);
-  v4i* sQ = reinterpret_cast<v4i*>(QREG ? s_mla : s_mla + 2 * TS * kTileBytes + NW * MG * 2 * 8 * 64 + Cfg::kHeadsWg * 4);
+  uint32_t(*sP)[MG][2][8][16] = reinterpret_cast<uint32_t(*)[MG][2][8][16]>(s_mla + Cfg::kSmall);
+  float* sAlpha = reinterpret_cast<float*>(s_mla + Cfg::kSmall + NW * MG * 2 * 8 * 64);
+  constexpr bool PIPE = TS == 1;  // scores one tile ahead (see below)
+  v4i* sQ = reinterpret_cast<v4i*>(s_mla);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 15, g = lane >> 4;
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   const int8_t* Cb = p.C + (int64_t)b * p.L * p.ld;
   const float* sc_tok = p.scale + (int64_t)b * p.L;  // per-token mode only
   const v4i zero4 = {0, 0, 0, 0};
-  uint8_t* tiles2 = sTiles + 2 * ts * kTileBytes;  // this stream's two tile buffers: tile k lives in buffer k & 1
+  uint8_t* tiles2 = sTiles + 2 * ts * kTileBytes;  // two streams: the two tile buffers of this one, tile k in buffer k & 1
   const int n_iter = (int)((max(t_end - t_begin, (int64_t)0) + TS * kTile - 1) / (TS * kTile));  // same for every wave
 
   // A-fragment row of this lane: slot j&3 of head pair j>>2 = (head, component)
@@ -201,14 +202,15 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   const int row_head = (j >> 2) * 2 + (slot >> 1);
   const int row_comp = slot & 1;
 
-  // ---- tile fetch, two tiles ahead of their use (two register sets).  The 64 WS lanes of a stream take one
+  // ---- tile fetch, two tiles ahead of their use (two register sets; one token stream: one set, and a third LDS
+  // buffer).  The 64 WS lanes of a stream take one
   // cached row per WS lanes: a lane fetches the 16-byte pieces fcol, fcol + WS, ... of its row, so the loads of a
   // lane share one base address and the LDS image needs no index arithmetic.  Fetches and LDS writes are
   // unconditional (rows past the end repeat the last valid one): straight-line code lets the compiler count
   // the loads in flight exactly, so the wait before an LDS write covers its own tile only.
   constexpr int LPR = Cfg::kLanesRow;
   const int frow = ((wave % WS) * 64 + lane) / LPR, fcol = ((wave % WS) * 64 + lane) % LPR;
-  v4i G[2][NLD];
+  v4i G[PIPE ? 1 : 2][NLD];
   auto fetch = [&](auto bufc, int it) __attribute__((always_inline)) {
     constexpr int BUF = decltype(bufc)::value;
     const int64_t t0 = t_begin + ((int64_t)it * TS + ts) * kTile;
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   using Buf1 = std::integral_constant<int, 1>;
   if (n_iter > 0) {
     fetch(Buf0{}, 0);
-    fetch(Buf1{}, 1);
+    if constexpr (!PIPE) fetch(Buf1{}, 1);
   }
 
   // ---- Alg. 3 steps 1-2 for the query rows of this workgroup: a wave decomposes kHeadsWg / NW heads (all
@@ -260,8 +262,8 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
       mx = wave_max(mx);
       const float alpha = mx > 0.f ? __fdiv_rn(mx, 127.0f) : 0.f;
       const float beta = __fdiv_rn(alpha, 254.0f);
-      // reciprocal route with exact-division fallback (same codes); needs a normal beta
-      const bool fast = beta >= 1.17549435e-38f;
+      // without a division per element (same codes) unless the row needs them
+      const bool fast = mx > 0.f && !needs_divisions(alpha, beta);
       const float ra = fast ? __fdiv_rn(1.0f, alpha) : 0.f, rb = fast ? __fdiv_rn(1.0f, beta) : 0.f;
       const int hq = hl % 8;  // head within its A fragment
       const int jrow = 4 * (hq >> 1) + 2 * (hq & 1);
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
         for (int e = 0; e < 4; ++e) {
           int c1 = 0, c2 = 0;
           if (fast)
-            int8_codes_fast(x[bi][e], alpha, ra, beta, rb, c1, c2);
+            int8_codes_by_reciprocal(x[bi][e], alpha, ra, beta, rb, c1, c2);
           else if (mx > 0.f)
             int8_codes(x[bi][e], alpha, beta, c1, c2);
           w1 |= ((uint32_t)c1 & 0xFFu) << (8 * e);
@@ -298,16 +300,14 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
       }
     }
   }
+  v4i qreg[MG][9];  // the A fragments
   if (!QFUSED) {  // codes and alpha_Q come from mla_q_decompose_kernel
 #pragma unroll
     for (int mg = 0; mg < MG; ++mg) {
-      if (ts == 0 && ch == 0) {
-        const int64_t qrow = (int64_t)b * Hq + min(hw + 8 * mg + row_head, Hq - 1);  // rows past Hq: results unused
-        const int8_t* src = (row_comp ? p.qc2 : p.qc1) + qrow * kLatK + 16 * g;
+      const int64_t qrow = (int64_t)b * Hq + min(hw + 8 * mg + row_head, Hq - 1);  // rows past Hq: results unused
+      const int8_t* src = (row_comp ? p.qc2 : p.qc1) + qrow * kLatK + 16 * g;
 #pragma unroll
-        for (int sc = 0; sc < 9; ++sc)
-          sQ[((hg * MG + mg) * 9 + sc) * 64 + lane] = *reinterpret_cast<const v4i*>(src + 64 * sc);
-      }
+      for (int sc = 0; sc < 9; ++sc) qreg[mg][sc] = *reinterpret_cast<const v4i*>(src + 64 * sc);
     }
     if (tid < Cfg::kHeadsWg) sAlpha[tid] = p.qalpha[(int64_t)b * Hq + min(hb + tid, Hq - 1)];
   }
@@ -320,16 +320,13 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
       aq[mg][hh] = sAlpha[Cfg::kHeadsWave * hg + 8 * mg + g * 2 + hh];
       bq[mg][hh] = __fdiv_rn(aq[mg][hh], 254.0f);
     }
-  // with registers to spare (few head groups) the fragments stay in registers instead
-  v4i qreg[MG][QREG ? 9 : 1];
-  if (QREG) {
+  if (QFUSED) {
 #pragma unroll
     for (int mg = 0; mg < MG; ++mg)
 #pragma unroll
-      for (int sc = 0; sc < 9; ++sc) qreg[mg][QREG ? sc : 0] = sQ[((hg * MG + mg) * 9 + sc) * 64 + lane];
+      for (int sc = 0; sc < 9; ++sc) qreg[mg][sc] = sQ[((hg * MG + mg) * 9 + sc) * 64 + lane];
     __syncthreads();  // the staging area is tile memory from here on
   }
-  const v4i* qsrc = sQ + (hg * MG * 9) * 64 + lane;  // fragment (mg, s) at qsrc[(mg * 9 + s) * 64]
 
   float m_run[MG][2], l_run[MG][2], o_run[MG][NSL][2][8];  // o_run[mg][slab][hh][c]: head 8 mg + 2 g + hh, channel 128 slab + 16 c + j
   float unit = 0.f;                   // 0: no coded tile yet
@@ -346,170 +343,191 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
         for (int c = 0; c < 8; ++c) o_run[mg][sl][hh][c] = 0.f;
     }
 
-  // LDS holds two tiles per stream, so a step needs one workgroup barrier: after it tile `it` is visible and
-  // nobody reads tile it - 1 any more, whose buffer then takes tile it + 1 from the registers while the loads
-  // of tiles it + 2 and it + 3 are in flight.
-  auto stage = [&](auto bufc, int k) __attribute__((always_inline)) {  // registers of tile k -> LDS buffer k & 1
+  // registers of tile k -> LDS buffer `dst`, and the fetch of the tile that takes their place
+  auto stage = [&](auto bufc, uint8_t* buf, int k_next) __attribute__((always_inline)) {
     constexpr int BUF = decltype(bufc)::value;
-    uint8_t* dst = tiles2 + BUF * kTileBytes + tile_row(frow) + 16 * (fcol ^ tile_swz(frow));  // LPR is a multiple of 4
+    uint8_t* dst = buf + tile_row(frow) + 16 * (fcol ^ tile_swz(frow));  // LPR is a multiple of 4
 #pragma unroll
     for (int i = 0; i < NLD; ++i)
       if (36 % LPR == 0 || fcol + LPR * i < 36) *reinterpret_cast<v4i*>(dst + 16 * LPR * i) = G[BUF][i];
-    fetch(bufc, k + 2);
+    fetch(bufc, k_next);
   };
-  auto step = [&](auto bufc, int it) __attribute__((always_inline)) {  // bufc: buffer of tile it + 1
-    constexpr int BUF = decltype(bufc)::value;
-    const uint8_t* tile = tiles2 + (1 - BUF) * kTileBytes;
-    const int64_t t0 = t_begin + ((int64_t)it * TS + ts) * kTile;
-    const bool tile_live = t0 < t_end;  // uniform over the waves of a stream
-    __syncthreads();
-    // the token scales of this tile: issued ahead of the next fetch, first used after the score product
-    float sk[4];
+  auto tile_begin = [&](int it) { return t_begin + ((int64_t)it * TS + ts) * kTile; };
+  auto load_scales = [&](int it, float (&sk)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) sk[tt] = PER_TOKEN ? sc_tok[min(t0 + 16 * tt + j, last)] : 1.f;
-    stage(bufc, it + 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!tile_live) return;
+    for (int tt = 0; tt < 4; ++tt) sk[tt] = PER_TOKEN ? sc_tok[min(tile_begin(it) + 16 * tt + j, last)] : 1.f;
+  };
 
-    bool live[4];
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt) live[tt] = t0 + 16 * tt + j < t_end;
-    // ---- (2) S1, S2 over the nine 64-channel chunks; a key fragment serves both A fragments
-    v4i sd[MG][4];
+  // ---- (2) S1, S2 of a tile over the nine 64-channel chunks; a key fragment serves both A fragments.  Software
+  // pipeline over the 36 (chunk, token group) fragments: LDS reads five fragments ahead.  `between(c)` is emitted
+  // after chunk c, so that its vector instructions issue under the chunk's MFMAs and LDS reads.
+  auto scores = [&](const uint8_t* tile, v4i (&sd)[MG][4], auto&& between) __attribute__((always_inline)) {
 #pragma unroll
     for (int mg = 0; mg < MG; ++mg)
 #pragma unroll
       for (int tt = 0; tt < 4; ++tt) sd[mg][tt] = zero4;
-    {
-      // software pipeline over the 36 (chunk, token group) fragments: LDS reads three fragments ahead
-      constexpr int NKF = 36, DEPTH = 4;
-      v4i kf[DEPTH];
-      v4i qf[2][MG];  // A fragments of the current and the next 64-channel chunk
-      const uint8_t* ksrc = tile + j * kPitch + 16 * (g ^ tile_swz(j));  // rows 16 tt + j share the swizzle of j
-      auto kload = [&](int i) __attribute__((always_inline)) {
-        kf[i % DEPTH] = *reinterpret_cast<const v4i*>(ksrc + tile_row(16 * (i % 4)) + 64 * (i / 4));
-      };
-      auto qload = [&](int sc) __attribute__((always_inline)) {
+    constexpr int NKF = 36, DEPTH = 6;
+    v4i kf[DEPTH];
+    const uint8_t* ksrc = tile + j * kPitch + 16 * (g ^ tile_swz(j));  // rows 16 tt + j share the swizzle of j
+    auto kload = [&](int i) __attribute__((always_inline)) {
+      kf[i % DEPTH] = *reinterpret_cast<const v4i*>(ksrc + tile_row(16 * (i % 4)) + 64 * (i / 4));
+    };
 #pragma unroll
-        for (int mg = 0; mg < MG; ++mg) qf[sc & 1][mg] = QREG ? qreg[mg][sc] : qsrc[(mg * 9 + sc) * 64];
-      };
-      qload(0);
+    for (int i = 0; i < DEPTH - 1; ++i) kload(i);
 #pragma unroll
-      for (int i = 0; i < DEPTH - 1; ++i) kload(i);
+    for (int i = 0; i < NKF; ++i) {
+      if (i + DEPTH - 1 < NKF) kload(i + DEPTH - 1);
 #pragma unroll
-      for (int i = 0; i < NKF; ++i) {
-        if (i + DEPTH - 1 < NKF) kload(i + DEPTH - 1);
-        if (i % 4 == 0 && i / 4 + 1 < 9) qload(i / 4 + 1);
-#pragma unroll
-        for (int mg = 0; mg < MG; ++mg) sd[mg][i % 4] = mfma_s8(qf[(i / 4) & 1][mg], kf[i % DEPTH], sd[mg][i % 4]);
+      for (int mg = 0; mg < MG; ++mg) sd[mg][i % 4] = mfma_s8(qreg[mg][i / 4], kf[i % DEPTH], sd[mg][i % 4]);
+      if (i % 4 == 3) {
+        between(i / 4);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (p.tap_s1 && ch == 0) {
+  };
+
+  // ---- (3)+(4) merge, online softmax, decomposition of P, in eight pieces for `between`
+  bool live[4];
+  float sv[4], ssk[4], sx[MG][2][4], mx[MG][2], corr[MG][2], rescale = 1.f;
+  bool coded = false;
+  v4i pa[MG];
+  auto soft = [&](int piece, int64_t t0, const v4i (&sd)[MG][4], const float (&sk)[4]) __attribute__((always_inline)) {
+    if (piece == 0) {
+      // scale of the P decomposition: alpha_P = top/127, top a bound on P (times the value scale): the largest
+      // value scale this wave has met so far (the untiled algorithm takes the largest of all tokens; a running
+      // maximum is never coarser than that and, being monotone, only ever shrinks the running output below)
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) {
+        live[tt] = t0 + 16 * tt + j < t_end;
+        sv[tt] = live[tt] ? sk[tt] : 0.f;
+        ssk[tt] = p.sm_scale_log2 * sk[tt];
+      }
+      if (PER_TOKEN) top = fmaxf(top, row16_max(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]))));
+      coded = top > 1e-30f;  // below that every code of the tile is zero
+      const float to_code = coded ? __fdiv_rn(127.0f, top) : 0.f;
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) sv[tt] *= to_code;  // from here on: value scale in units of alpha_P
+    }
+    if (piece == 1) {
+      // The running output is kept in units of `unit` = alpha_P / 254, so that a tile's contribution is the
+      // integer 254 O1 + O2 itself; a growing alpha_P rescales the running output (by a factor <= 1) together
+      // with the softmax correction.
+      rescale = 1.f;
+      if (coded) {
+        const float unit_new = top * (1.0f / (127.0f * 254.0f));
+        rescale = unit > 0.f ? __fdiv_rn(unit, unit_new) : 0.f;  // nothing accumulated before the first coded tile
+        unit = unit_new;
+      }
+    }
+    if (piece == 2 || piece == 3) {
+      const int hh = piece - 2;
+#pragma unroll
+      for (int mg = 0; mg < MG; ++mg) {
+        mx[mg][hh] = -INFINITY;
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+          const float v = (aq[mg][hh] * (float)sd[mg][tt][2 * hh] + bq[mg][hh] * (float)sd[mg][tt][2 * hh + 1]) * ssk[tt];
+          sx[mg][hh][tt] = live[tt] ? v : -INFINITY;
+          mx[mg][hh] = fmaxf(mx[mg][hh], sx[mg][hh][tt]);
+        }
+      }
+    }
+    if (piece == 4) {
 #pragma unroll
       for (int mg = 0; mg < MG; ++mg)
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-          const int head = hw + 8 * mg + g * 2 + hh;
-          if (head < Hq) {
-            const int64_t row = ((int64_t)b * Hq + head) * p.L;
-#pragma unroll
-            for (int tt = 0; tt < 4; ++tt)
-              if (live[tt]) {
-                p.tap_s1[row + t0 + 16 * tt + j] = sd[mg][tt][2 * hh];
-                p.tap_s2[row + t0 + 16 * tt + j] = sd[mg][tt][2 * hh + 1];
-              }
-          }
+          const float m_new = fmaxf(m_run[mg][hh], row16_max(mx[mg][hh]));
+          const float cr = __builtin_amdgcn_exp2f(m_run[mg][hh] - m_new);
+          corr[mg][hh] = cr * rescale;
+          m_run[mg][hh] = m_new;
+          l_run[mg][hh] *= cr;
         }
     }
-    // scale of the P decomposition: alpha_P = top/127, top a bound on P (times the value scale): the largest
-    // value scale this wave has met so far (the untiled algorithm takes the largest of all tokens; a running
-    // maximum is never coarser than that and, being monotone, only ever shrinks the running output below)
-    float sv[4];
+    if (piece == 5 || piece == 6) {
+      // P (times the value scale) in units of alpha_P, v in [0, 127], as v = c1 + c2 / 254: adding 1.5 * 2^23 rounds
+      // to the nearest integer (ties to even) and leaves the code in the low byte; the rest r = v - c1 is exact and
+      // 254 r is rounded once.  |c1| <= 127 and |254 r| <= 127: nothing to clamp.
+      constexpr float kMagic = 12582912.0f;
+      const int hh = piece - 5;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) sv[tt] = live[tt] ? sk[tt] : 0.f;
-    if (PER_TOKEN) top = fmaxf(top, row16_max(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]))));
-    const bool coded = top > 1e-30f;  // below that every code of the tile is zero
-    const float to_code = coded ? __fdiv_rn(127.0f, top) : 0.f;
-    // The running output is kept in units of `unit` = alpha_P / 254, so that a tile's contribution is the
-    // integer 254 O1 + O2 itself; a growing alpha_P rescales the running output (by a factor <= 1) together
-    // with the softmax correction.
-    float rescale = 1.f;
-    if (coded) {
-      const float unit_new = top * (1.0f / (127.0f * 254.0f));
-      rescale = unit > 0.f ? __fdiv_rn(unit, unit_new) : 0.f;  // nothing accumulated before the first coded tile
-      unit = unit_new;
+      for (int mg = 0; mg < MG; ++mg) {
+        uint32_t c1[4], c2[4];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+          const float pr = __builtin_amdgcn_exp2f(sx[mg][hh][tt] - m_run[mg][hh]);
+          l_run[mg][hh] += pr;
+          const float v = pr * sv[tt];
+          const float a = v + kMagic;
+          c1[tt] = __float_as_uint(a);
+          c2[tt] = __float_as_uint(__builtin_fmaf(v - (a - kMagic), 254.0f, kMagic));
+        }
+        auto low_bytes = [](const uint32_t (&c)[4]) {
+          return __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[3], c[2], 0x0c0c0400u), __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0400u),
+                                       0x05040100u);
+        };
+        sP[wave][mg][0][g * 2 + hh][j] = low_bytes(c1);
+        sP[wave][mg][1][g * 2 + hh][j] = low_bytes(c2);
+      }
     }
-    // ---- (3)+(4) merge, online softmax, decompose P
-    float corr[MG][2];
+    if (piece == 7) {  // into A-fragment order through LDS of the wave's own
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int mg = 0; mg < MG; ++mg) pa[mg] = *reinterpret_cast<const v4i*>(&sP[wave][mg][row_comp][row_head][4 * g]);
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+
+  auto tap_scores = [&](int64_t t0, const v4i (&sd)[MG][4]) __attribute__((always_inline)) {
+    if (!(p.tap_s1 && ch == 0)) return;
 #pragma unroll
     for (int mg = 0; mg < MG; ++mg)
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
-        float s[4];
-        float mx = -INFINITY;
+        const int head = hw + 8 * mg + g * 2 + hh;
+        if (head < Hq) {
+          const int64_t row = ((int64_t)b * Hq + head) * p.L;
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-          const float v = (aq[mg][hh] * (float)sd[mg][tt][2 * hh] + bq[mg][hh] * (float)sd[mg][tt][2 * hh + 1]) *
-                          (p.sm_scale_log2 * sk[tt]);
-          s[tt] = live[tt] ? v : -INFINITY;
-          mx = fmaxf(mx, s[tt]);
+          for (int tt = 0; tt < 4; ++tt)
+            if (t0 + 16 * tt + j < t_end) {
+              p.tap_s1[row + t0 + 16 * tt + j] = sd[mg][tt][2 * hh];
+              p.tap_s2[row + t0 + 16 * tt + j] = sd[mg][tt][2 * hh + 1];
+            }
         }
-        mx = row16_max(mx);
-        const float m_new = fmaxf(m_run[mg][hh], mx);
-        const float cr = __builtin_amdgcn_exp2f(m_run[mg][hh] - m_new);
-        corr[mg][hh] = cr * rescale;
-        m_run[mg][hh] = m_new;
-        float lsum = 0.f;
-        uint32_t w1 = 0, w2 = 0;
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-          const float pr = __builtin_amdgcn_exp2f(s[tt] - m_new);
-          lsum += pr;
-          const float t = pr * sv[tt] * to_code;
-          const float c1 = fminf(rintf(t), 127.f);
-          const float c2 = fminf(fmaxf(rintf((t - c1) * 254.0f), -127.f), 127.f);
-          w1 |= ((uint32_t)(int)c1 & 0xFFu) << (8 * tt);
-          w2 |= ((uint32_t)(int)c2 & 0xFFu) << (8 * tt);
-        }
-        l_run[mg][hh] = l_run[mg][hh] * cr + lsum;
-        sP[wave][mg][0][g * 2 + hh][j] = w1;
-        sP[wave][mg][1][g * 2 + hh][j] = w2;
       }
-    __builtin_amdgcn_wave_barrier();
-    v4i pa[MG];
-#pragma unroll
-    for (int mg = 0; mg < MG; ++mg) pa[mg] = *reinterpret_cast<const v4i*>(&sP[wave][mg][row_comp][row_head][4 * g]);
-    __builtin_amdgcn_wave_barrier();
-    // ---- (5) O1, O2 over this wave's 128-channel slabs of the same rows.  The B operand (64 tokens x 16
-    // channels) comes from two transposing LDS reads: in each 16-lane group, source lane s points at 8
-    // channel bytes of one token, and lane n receives byte n&7 of the eight source lanes 2k + (n>>3); with
-    // even source lanes on channels 0..7 and odd ones on channels 8..15 of token(k), lane n ends up with
-    // channel n of eight tokens.  token(k) follows the packing of the P codes (word 4g+i, byte t <-> token
-    // 16 t + 4 g + i).
+  };
+
+  // ---- (5) O1, O2 over this wave's 128-channel slabs of the same rows.  The B operand (64 tokens x 16
+  // channels) comes from two transposing LDS reads: in each 16-lane group, source lane s points at 8
+  // channel bytes of one token, and lane n receives byte n&7 of the eight source lanes 2k + (n>>3); with
+  // even source lanes on channels 0..7 and odd ones on channels 8..15 of token(k), lane n ends up with
+  // channel n of eight tokens.  token(k) follows the packing of the P codes (word 4g+i, byte t <-> token
+  // 16 t + 4 g + i).
+  auto output = [&](const uint8_t* tile) __attribute__((always_inline)) {
     const int vk = j >> 1;
     // rows 16 (vk & 3) + 4 g + (vk >> 2) (+ 2 for the second read): all in 4-row group g of their 16 rows
     const uint8_t* vsrc = tile + tile_row(16 * (vk & 3) + 4 * g + (vk >> 2)) + 8 * (j & 1);
     int vcol[4];  // byte offset of 16-byte column c within its group of four, c = 0..3
 #pragma unroll
     for (int c = 0; c < 4; ++c) vcol[c] = 16 * (c ^ tile_swz(4 * g));
-    // Software pipeline over the 16-channel blocks: LDS reads two blocks ahead, the two MFMAs of a block
+    // Software pipeline over the 16-channel blocks: LDS reads four blocks ahead, the two MFMAs of a block
     // issued one block before their results are merged on the vector ALU.
     constexpr int NST = NSL * 8;
-    v2i rb[3][2];
+    constexpr int AHEAD = 4;
+    v2i rb[AHEAD + 1][2];
     v4i acc[2][MG];
     auto vload = [&](int st) __attribute__((always_inline)) {
       const uint8_t* src = vsrc + 128 * (ch * NSL + st / 8) + 64 * ((st % 8) / 4) + vcol[st % 4];
-      rb[st % 3][0] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i*)src);
-      rb[st % 3][1] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i*)(src + 2 * kPitch));
+      rb[st % (AHEAD + 1)][0] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i*)src);
+      rb[st % (AHEAD + 1)][1] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i*)(src + 2 * kPitch));
     };
-    vload(0);
-    vload(1);
+#pragma unroll
+    for (int st = 0; st < AHEAD; ++st) vload(st);
 #pragma unroll
     for (int st = 0; st <= NST; ++st) {
-      if (st + 2 < NST) vload(st + 2);
+      if (st + AHEAD < NST) vload(st + AHEAD);
       if (st < NST) {
-        const v4i bf = {rb[st % 3][0][0], rb[st % 3][0][1], rb[st % 3][1][0], rb[st % 3][1][1]};
+        const v4i bf = {rb[st % (AHEAD + 1)][0][0], rb[st % (AHEAD + 1)][0][1], rb[st % (AHEAD + 1)][1][0], rb[st % (AHEAD + 1)][1][1]};
 #pragma unroll
         for (int mg = 0; mg < MG; ++mg) acc[st & 1][mg] = mfma_s8(pa[mg], bf, zero4);
       }
@@ -528,10 +546,74 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  if (n_iter > 0) stage(Buf0{}, 0);
-  for (int it = 0; it < n_iter; it += 2) {  // an odd count is padded with a tile past the end
-    step(Buf1{}, it);
-    step(Buf0{}, it + 1);
+
+  if constexpr (PIPE) {
+    // One token stream, three tile buffers: the scores of tile it + 1 are computed around the softmax of tile it, so
+    // that the MFMAs and LDS reads of the one run under the vector instructions of the other (the two waves of a
+    // SIMD pass the barrier together and would otherwise be in the same phase all the time).  After the barrier of
+    // a step tile it + 1 is visible and nobody reads tile it - 1 any more, whose buffer takes tile it + 2 from the
+    // registers while the loads of tile it + 3 are in flight.  What bounds it: the issue of about 450 vector and 70
+    // matrix instructions per wave and tile, two waves per SIMD (5.9 kcycles per tile of 64 heads; before, with the
+    // phases in turn, 9.3).  32 x 4096 tokens, 128 heads 81.3 -> 76.5 us (floor by its 73 G operations 24); 32 heads
+    // 44.3 -> 38.3.  Filling LDS without registers (global_load_lds) measured 79.3, wave priorities that keep the two
+    // waves of a SIMD in different phases no difference.
+    uint8_t *cur = sTiles, *nxt = sTiles + kTileBytes, *spare = sTiles + 2 * kTileBytes;
+    v4i sd[MG][4], sd_next[MG][4];
+    float sk[4], sk_next[4];
+    if (n_iter > 0) {
+      load_scales(0, sk);
+      stage(Buf0{}, cur, 1);
+      stage(Buf0{}, nxt, 2);
+      __syncthreads();
+      scores(cur, sd, [](int) {});
+      tap_scores(t_begin, sd);
+    }
+    for (int it = 0; it < n_iter; ++it) {
+      const int64_t t0 = tile_begin(it);
+      if (it > 0) __syncthreads();
+      load_scales(it + 1, sk_next);
+      stage(Buf0{}, spare, it + 3);
+      __builtin_amdgcn_sched_barrier(0);
+      scores(nxt, sd_next, [&](int c) __attribute__((always_inline)) { soft(c, t0, sd, sk); });
+      tap_scores(t0 + kTile, sd_next);
+      output(cur);
+      uint8_t* done = cur;
+      cur = nxt, nxt = spare, spare = done;
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) {
+        sk[tt] = sk_next[tt];
+#pragma unroll
+        for (int mg = 0; mg < MG; ++mg) sd[mg][tt] = sd_next[mg][tt];
+      }
+    }
+  } else {
+    // Two streams, two tiles each: a step needs one workgroup barrier; after it tile `it` is visible and
+    // nobody reads tile it - 1 any more, whose buffer then takes tile it + 1 from the registers while the loads
+    // of tiles it + 2 and it + 3 are in flight.
+    auto step = [&](auto bufc, int it) __attribute__((always_inline)) {  // bufc: buffer of tile it + 1
+      constexpr int BUF = decltype(bufc)::value;
+      const uint8_t* tile = tiles2 + (1 - BUF) * kTileBytes;
+      const int64_t t0 = tile_begin(it);
+      const bool tile_live = t0 < t_end;  // uniform over the waves of a stream
+      __syncthreads();
+      // the token scales of this tile: issued ahead of the next fetch, first used after the score product
+      float sk[4];
+      load_scales(it, sk);
+      stage(bufc, tiles2 + BUF * kTileBytes, it + 3);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!tile_live) return;
+      v4i sd[MG][4];
+      scores(tile, sd, [](int) {});
+      tap_scores(t0, sd);
+#pragma unroll
+      for (int piece = 0; piece < 8; ++piece) soft(piece, t0, sd, sk);
+      output(tile);
+    };
+    if (n_iter > 0) stage(Buf0{}, tiles2, 2);
+    for (int it = 0; it < n_iter; it += 2) {  // an odd count is padded with a tile past the end
+      step(Buf1{}, it);
+      step(Buf0{}, it + 1);
+    }
   }
 
   float lsum[MG][2];
@@ -544,7 +626,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
     // stream 1 hand (m, l, O) to the waves of stream 0 that hold the same heads and channels, lane by lane, so
     // that a split writes one partial instead of two (half the partial-result traffic of the call)
     constexpr int NV = MG * 2 * (2 + NSL * 8);  // floats per lane
-    static_assert((size_t)WS * NV * 64 * 4 <= (size_t)2 * TS * kTileBytes, "exchange area");
+    static_assert((size_t)WS * NV * 64 * 4 <= (size_t)Cfg::kBufs * TS * kTileBytes, "exchange area");
     float* xch = reinterpret_cast<float*>(sTiles) + (wave % WS) * NV * 64 + lane;
     // each stream keeps its output in its own unit (the alpha_P / 254 of its last coded tile): plain values from here
 #pragma unroll
@@ -592,39 +674,50 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
   }
   // ---- the partial (m, l, O) of this wave's heads and value channels: one per KV split
   static_assert(TS <= 2, "token streams are merged pairwise above");
+  if (p.nparts == 1) {
+#pragma unroll
+    for (int sl = 0; sl < NSL; ++sl) {
+      float vs[8];  // fetched ahead of the stores, or each of them would wait for its own
+#pragma unroll
+      for (int c = 0; c < 8; ++c) vs[c] = PER_TOKEN ? 1.f : p.scale[128 * (ch * NSL + sl) + 16 * c + j];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(vs[c]));
+#pragma unroll
+      for (int mg = 0; mg < MG; ++mg)
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          const int head = hw + 8 * mg + g * 2 + hh;
+          if (head >= Hq) continue;
+          const int64_t at = ((int64_t)b * Hq + head) * kLatV + 128 * (ch * NSL + sl) + j;
+          const float norm = lsum[mg][hh] > 0.f ? __fdiv_rn(unit, lsum[mg][hh]) : 0.f;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            float v = o_run[mg][sl][hh][c] * norm;
+            if (!PER_TOKEN) v *= vs[c];
+            if (p.out_bf16)
+              reinterpret_cast<uint16_t*>(p.out)[at + 16 * c] = f32_to_bf16_bits(v);
+            else
+              reinterpret_cast<float*>(p.out)[at + 16 * c] = v;
+          }
+        }
+    }
+    return;
+  }
 #pragma unroll
   for (int mg = 0; mg < MG; ++mg)
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const float l = lsum[mg][hh];
       const int head = hw + 8 * mg + g * 2 + hh;
       if (head >= Hq) continue;
-      if (p.nparts == 1) {
-        const int64_t orow = (int64_t)b * Hq + head;
-        const float norm = l > 0.f ? __fdiv_rn(unit, l) : 0.f;
+      const int64_t pr = (int64_t)blockIdx.x * Hq + head;  // nparts == nsplit
 #pragma unroll
-        for (int sl = 0; sl < NSL; ++sl)
+      for (int sl = 0; sl < NSL; ++sl)
 #pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            const int col = 128 * (ch * NSL + sl) + 16 * c + j;
-            float v = o_run[mg][sl][hh][c] * norm;
-            if (!PER_TOKEN) v *= p.scale[col];
-            if (p.out_bf16)
-              reinterpret_cast<uint16_t*>(p.out)[orow * kLatV + col] = f32_to_bf16_bits(v);
-            else
-              reinterpret_cast<float*>(p.out)[orow * kLatV + col] = v;
-          }
-      } else {
-        const int64_t pr = (int64_t)blockIdx.x * Hq + head;  // nparts == nsplit
-#pragma unroll
-        for (int sl = 0; sl < NSL; ++sl)
-#pragma unroll
-          for (int c = 0; c < 8; ++c)
-            p.part_o[pr * kLatV + 128 * (ch * NSL + sl) + 16 * c + j] = o_run[mg][sl][hh][c] * unit;
-        if (ch == 0 && j == 0) {
-          p.part_m[pr] = m_run[mg][hh];
-          p.part_l[pr] = l;
-        }
+        for (int c = 0; c < 8; ++c)
+          p.part_o[pr * kLatV + 128 * (ch * NSL + sl) + 16 * c + j] = o_run[mg][sl][hh][c] * unit;
+      if (ch == 0 && j == 0) {
+        p.part_m[pr] = m_run[mg][hh];
+        p.part_l[pr] = lsum[mg][hh];
       }
     }
 }

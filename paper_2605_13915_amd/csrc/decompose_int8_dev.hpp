@@ -57,27 +57,6 @@ __device__ __forceinline__ void chunk_codes(const Chunk16& c, float alpha, float
   o2 = make_uint4(b[0], b[1], b[2], b[3]);
 }
 
-// Bit-exact quantisation without a division per element.  q = rne(x/alpha) is computed as
-// rne(x * (1/alpha)); the product differs from the correctly rounded quotient by at most
-// 127.49*2^-22 < 3.1e-5 in absolute terms (|x/alpha| <= 127.49 for either pair of range constants), so the two can round differently only if the product is
-// within that distance of a half-integer.  Lanes where it is within 1e-4 recompute with the
-// exact division (about 2 elements in 10^4).  Same for the residual pass.
-__device__ __forceinline__ void int8_codes_fast(float x, float alpha, float ra, float beta, float rb,
-                                                int& c1, int& c2) {
-  float t = x * ra;
-  float q = rintf(t);
-  const bool tie1 = fabsf(t - q) > 0.5f - 1e-4f;
-  if (__builtin_amdgcn_ballot_w64(tie1) != 0)  // wave-uniform branch: the division is really skipped
-    q = tie1 ? rintf(__fdiv_rn(x, alpha)) : q;
-  const float r = __fmaf_rn(-alpha, q, x);
-  float u = r * rb;
-  float p = rintf(u);
-  const bool tie2 = fabsf(u - p) > 0.5f - 1e-4f;
-  if (__builtin_amdgcn_ballot_w64(tie2) != 0) p = tie2 ? rintf(__fdiv_rn(r, beta)) : p;
-  c1 = (int)fminf(fmaxf(q, -128.f), 127.f);
-  c2 = (int)fminf(fmaxf(p, -128.f), 127.f);
-}
-
 // Correctly rounded x / a without a division: t = x * RN(1/a) is within two units in the last place of
 // the quotient; one refinement with the exact FMA residual, t' = t + (x - a t) * RN(1/a), makes it faithful,
 // and a second one then returns RN(x / a) itself (Markstein's theorem on FMA division: exact whenever the
@@ -89,6 +68,15 @@ __device__ __forceinline__ float quotient_rn(float x, float a, float ra) {
   t = __fmaf_rn(__fmaf_rn(-a, t, x), ra, t);
   t = __fmaf_rn(__fmaf_rn(-a, t, x), ra, t);
   return t;
+}
+
+// The codes of one element without a division; alpha and beta as for quad_codes_fast.
+__device__ __forceinline__ void int8_codes_by_reciprocal(float x, float alpha, float ra, float beta, float rb, int& c1,
+                                                         int& c2) {
+  const float q = rintf(quotient_rn(x, alpha, ra));
+  const float p = rintf(quotient_rn(__fmaf_rn(-alpha, q, x), beta, rb));
+  c1 = (int)q;
+  c2 = (int)p;
 }
 
 __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
