@@ -13,7 +13,8 @@
 //       dword per lane; a wave reads the bytes of its fragments and picks one with the instruction's op_sel.
 //   (2) transpose_w_scales_kernel: the weights' E8M0 bytes [N][K/32] -> sw_t in the same layout
 //       over columns (the weight values themselves are consumed where they are).
-//   (3) gemm_w4_dma_kernel: 256 x 256 output tile, 8 waves of 64 x 128, one K step = 64 elements
+//   (3) gemm_w4_small_kernel where the output has few 256 x 256 tiles, else
+//       gemm_w4_dma_kernel: 256 x 256 output tile, 8 waves of 64 x 128, one K step = 64 elements
 //       = two MX blocks = exactly one MFMA K extent (lane l: row/column l%32, block l/32).  A stage
 //       is 33 KB: 24 KB activation operands, 8 KB weights, 1 KB scale bytes, filled by 40
 //       global_load_lds_dwordx4 instructions (5 per wave: three activation kilobytes, one weight kilobyte,
@@ -490,6 +491,198 @@ __global__ __launch_bounds__(512) void gemm_w4_dma_kernel(GemmW4PrefillArgs a, i
     }
 }
 
+// ------------------------------------------------------------------ (4) GEMM on small tiles
+// The same product on tiles of 32 GM x 32 GN for calls whose 256 x 256 tiles leave most of the chip idle.  Operands,
+// layouts and accumulation order are those of gemm_w4_dma_kernel (same bits).  A stage holds KD K steps; the tiles are
+// small, so two workgroups (or eight waves) share a CU and hide each other's barriers and the fragment reads need no
+// pipeline.  What bounds it: the latency of the fills, about 0.5 us per stage of 128 values of K (more stages in flight
+// measured no better); 256 x 4096 x 4096 53.9 -> 23.6 us, 278 x 1536 x 1440 30.5 -> 13.5, 1024 x 4096 x 4096 57.6 -> 38.8.
+template <int N_LANES>
+__device__ __forceinline__ void w4_lds_dma16_first(const uint8_t* gbase, uint32_t voff, uint32_t lds_addr) {
+  const uint64_t g = reinterpret_cast<uint64_t>(gbase);
+  const uint32_t glo = __builtin_amdgcn_readfirstlane((uint32_t)g), ghi = __builtin_amdgcn_readfirstlane((uint32_t)(g >> 32));
+  gbase = reinterpret_cast<const uint8_t*>(((uint64_t)ghi << 32) | glo);
+  lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+  uint64_t saved;
+  asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, %0"
+               : "=&s"(saved)
+               : "v"(voff), "s"(gbase), "s"(lds_addr), "n"((1 << N_LANES) - 1)
+               : "memory", "m0");
+}
+
+template <int GM, int GN, int WM, int WN, int KD, int NS>
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_w4_small_kernel(GemmW4PrefillArgs a, int tiles_m, int tiles_n) {
+  constexpr int NW = WM * WN, FI = GM / WM, FJ = GN / WN;
+  constexpr int SZ_A = GM * 3072, SZ_W = GN * 1024, SZ_S = 512, STEP = SZ_A + SZ_W + SZ_S, STAGE = KD * STEP;
+  constexpr int PER_STEP = 3 * GM + GN;      // kilobytes of operands per K step
+  constexpr int Q = PER_STEP * KD / NW;      // fill instructions per wave and stage, and one for the scale bytes
+  constexpr int L = Q + 1;
+  constexpr int S_LANES = 32 * KD / NW;      // 16-byte pieces of scale bytes per wave and stage
+  static_assert(PER_STEP * KD % NW == 0 && 32 * KD % NW == 0 && S_LANES < 32, "fill split");
+  static_assert(GM <= 4 && GN <= 4 && FI <= 2 && FJ <= 2 && GM % WM == 0 && GN % WN == 0, "one 128-row half of scale bytes");
+  static_assert(NS >= 3 && (NS - 2) * L < 64, "stage count");
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem4s[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int l32 = lane & 31, kb = lane >> 5;
+  const int64_t M = a.M, N = a.N;
+  const int KT = (int)(a.K / 64), stages = (KT + KD - 1) / KD;
+  const int total = tiles_m * tiles_n;
+  int id = blockIdx.x;
+  {
+    const int per_xcd = (total + 7) / 8;
+    id = (id % 8) * per_xcd + id / 8;
+  }
+  if (id >= total) return;
+  const int group = id / (kW4PGroupM * tiles_n);
+  const int first_m = group * kW4PGroupM;
+  const int rows_in_group = min(kW4PGroupM, tiles_m - first_m);
+  const int in_group = id - group * kW4PGroupM * tiles_n;
+  const int tm = first_m + in_group % rows_in_group;
+  const int tn = in_group / rows_in_group;
+  const int64_t m0 = (int64_t)tm * (32 * GM), n0 = (int64_t)tn * (32 * GN);
+
+  // fill instruction idx = q * NW + wave: K step idx / PER_STEP of the stage, then the activation kilobytes (contiguous
+  // in qop), then the weight groups of 32 columns (see gemm_w4_dma_kernel for the sources)
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem4s;
+  const int64_t row_w = a.K / 2, wtiles = (N + 15) / 16, wq = wtiles * 1024;
+  const int64_t a_step = a.Mpad * 96, s_step_a = a.Mpad * 2, s_step_w = a.Npad * 2;
+  const uint8_t* src[Q];
+  uint32_t voff[Q], dst[Q];
+  int64_t pair[Q], odd[Q];  // bytes between pairs of K steps, and from the even to the odd step of a pair
+  int kd[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int idx = q * NW + wave, p = idx % PER_STEP;
+    kd[q] = idx / PER_STEP;
+    dst[q] = lds0 + kd[q] * STEP + p * 1024;
+    if (p < 3 * GM) {
+      src[q] = a.qop + (m0 / 32 * 3 + p) * 1024;
+      voff[q] = lane * 16;
+      pair[q] = 2 * a_step, odd[q] = a_step;
+    } else {
+      const int wg = p - 3 * GM;
+      if (a.w_packed) {
+        src[q] = a.W + (n0 / 16) * 1024;
+        voff[q] = (uint32_t)((min(n0 / 16 + 2 * wg + (l32 >> 4), wtiles - 1) - n0 / 16) * 1024 + (kb * 16 + (l32 & 15)) * 16);
+        pair[q] = wq, odd[q] = 512;
+      } else {
+        src[q] = a.W + n0 * row_w;
+        voff[q] = (uint32_t)((min(n0 + 32 * wg + l32, N - 1) - n0) * row_w + kb * 16);
+        pair[q] = 64, odd[q] = 32;
+      }
+    }
+  }
+  // scale bytes of a K step: 256 of the 128 rows around the tile, 256 of the 128 columns, in pieces of 16
+  const int sp = wave * S_LANES + lane % S_LANES, s_kd = sp >> 5, s_w = (sp >> 4) & 1;
+  static_assert(S_LANES <= 16, "a wave's pieces are of one kind");
+  const int64_t s_step = __builtin_amdgcn_readfirstlane(s_w) ? s_step_w : s_step_a;
+  const uint8_t* s_src = __builtin_amdgcn_readfirstlane(s_w) ? a.sw_t + (n0 >> 7) * 256 : a.sa_t + (m0 >> 7) * 256;
+  const uint32_t s_voff = (uint32_t)((sp & 15) * 16);
+  const int s_step_of = __builtin_amdgcn_readfirstlane(s_kd);
+  const uint32_t s_dst = lds0 + s_step_of * STEP + SZ_A + SZ_W + (uint32_t)__builtin_amdgcn_readfirstlane((wave * S_LANES) & 31) * 16;
+  auto issue = [&](int st) {
+    const uint32_t buf = (uint32_t)((st % NS) * STAGE);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int kt = min(st * KD + kd[q], KT - 1);  // a last stage may hold fewer steps: the surplus is not read
+      w4_lds_dma16(src[q] + (int64_t)(kt >> 1) * pair[q] + (kt & 1) * odd[q], voff[q], dst[q] + buf);
+    }
+    w4_lds_dma16_first<S_LANES>(s_src + (int64_t)min(st * KD + s_step_of, KT - 1) * s_step, s_voff, s_dst + buf);
+  };
+
+  v16f acc[FI][FJ];
+#pragma unroll
+  for (int i = 0; i < FI; ++i)
+#pragma unroll
+    for (int j = 0; j < FJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  // the tile's fragments start at fragment (m0 / 32) % 4 of their 128-row half
+  const uint32_t o_sa = SZ_A + SZ_W + kb * 128 + l32 * 4 + (uint32_t)((m0 >> 5) & 3) + wm * FI;
+  const uint32_t o_sb = SZ_A + SZ_W + 256 + kb * 128 + l32 * 4 + (uint32_t)((n0 >> 5) & 3) + wn * FJ;
+  const int beta_shift = a.mv.shift * 0x0101;
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < stages) issue(t);
+  for (int st = 0; st < stages; ++st) {
+    const int younger = min(stages - 1, st + NS - 2) - st;
+    if (younger == NS - 2) w4_wait_vm_barrier<(NS - 2) * L>();
+    else if (younger == NS - 3) w4_wait_vm_barrier<(NS - 3) * L>();
+    else w4_wait_vm_barrier<0>();
+    if (st + NS - 1 < stages) issue(st + NS - 1);  // into the stage every wave has left
+#pragma unroll
+    for (int k = 0; k < KD; ++k) {
+      if (KD > 1 && st * KD + k >= KT) break;
+      const uint8_t* base = smem4s + (st % NS) * STAGE + k * STEP;
+      const int sa = FI == 1 ? (int)base[o_sa] : (int)*reinterpret_cast<const uint16_t*>(base + o_sa);
+      const int sb = FJ == 1 ? (int)base[o_sb] : (int)*reinterpret_cast<const uint16_t*>(base + o_sb);
+      v8i fb[FJ], fa[2][FI];
+#pragma unroll
+      for (int j = 0; j < FJ; ++j) {
+        const uint4 v = *reinterpret_cast<const uint4*>(base + SZ_A + (wn * FJ + j) * 1024 + lane * 16);
+        fb[j] = v8i{(int)v.x, (int)v.y, (int)v.z, (int)v.w, 0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < FI; ++i) {
+          const uint8_t* f = base + (wm * FI + i) * 3072 + c * 1536;
+          const uint4 v = *reinterpret_cast<const uint4*>(f + lane * 16);
+          const uint2 t = *reinterpret_cast<const uint2*>(f + 1024 + lane * 8);
+          fa[c][i] = v8i{(int)v.x, (int)v.y, (int)v.z, (int)v.w, (int)t.x, (int)t.y, 0, 0};
+        }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int s = c ? sa - beta_shift : sa;
+        acc[0][0] = mfma64_scaled<0, 0>(fa[c][0], fb[0], acc[0][0], s, sb);
+        if constexpr (FJ > 1) acc[0][FJ - 1] = mfma64_scaled<0, FJ - 1>(fa[c][0], fb[FJ - 1], acc[0][FJ - 1], s, sb);
+        if constexpr (FI > 1) acc[FI - 1][0] = mfma64_scaled<FI - 1, 0>(fa[c][FI - 1], fb[0], acc[FI - 1][0], s, sb);
+        if constexpr (FI > 1 && FJ > 1)
+          acc[FI - 1][FJ - 1] = mfma64_scaled<FI - 1, FJ - 1>(fa[c][FI - 1], fb[FJ - 1], acc[FI - 1][FJ - 1], s, sb);
+      }
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < FI; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t m = m0 + (wm * FI + i) * 32 + (r >> 2) * 8 + kb * 4 + (r & 3);
+      if (m < M) {
+#pragma unroll
+        for (int j = 0; j < FJ; ++j) {
+          const int64_t n = n0 + (wn * FJ + j) * 32 + l32;
+          if (n >= N) continue;
+          if (a.out_bf16)
+            __builtin_nontemporal_store(f32_to_bf16_bits(acc[i][j][r]), reinterpret_cast<uint16_t*>(a.y) + m * a.ldy + n);
+          else
+            __builtin_nontemporal_store(acc[i][j][r], reinterpret_cast<float*>(a.y) + m * a.ldy + n);
+        }
+      }
+    }
+}
+
+template <int GM, int GN, int WM, int WN, int KD, int NS>
+static int launch_w4_small(const GemmW4PrefillArgs& a, hipStream_t stream) {
+  const int tiles_m = (int)cdiv(a.M, 32 * GM), tiles_n = (int)cdiv(a.N, 32 * GN);
+  const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
+  constexpr size_t lds = (size_t)NS * KD * (GM * 3072 + GN * 1024 + 512);
+  static_assert(lds <= 160 * 1024, "LDS budget");
+  static bool attr_set = false;
+  if (!attr_set) {
+    MSD_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_w4_small_kernel<GM, GN, WM, WN, KD, NS>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((gemm_w4_small_kernel<GM, GN, WM, WN, KD, NS>), dim3(grid), dim3(WM * WN * 64), lds, stream, a, tiles_m, tiles_n);
+  MSD_LAUNCH_CHECK();
+  return MSD_OK;
+}
+
 // ------------------------------------------------------------------ host side
 bool gemm_w4_prefill_applies(int64_t M, int64_t K, int64_t N) {
   (void)N;
@@ -570,6 +763,14 @@ int launch_gemm_w4_prefill(const uint16_t* x, int64_t ldx, const uint8_t* W, con
   a.Mpad = (int64_t)l.Mpad;
   a.Npad = (int64_t)l.Npad;
   a.mv = mv;
+  // Tiles of 64 x 64 while two of them per CU cover the output, tiles of 128 x 128 (eight waves) while one per CU does,
+  // else the 256 x 256 tile, which reads the fewest operand bytes.  us at 64 / 128 / 256: 256 x 4096 x 4096 (256 tiles of
+  // 64) 24 / 34 / 54, 512 x 4096 x 4096 (512) 32 / 36 / 57, 1024 x 4096 x 4096 (256 of 128) 54 / 39 / 58, 1200 x 4096 x
+  // 4096 (320 of 128) 68 / 66 / 59, 206 x 1536 x 4480 15 / 17 / 29.  (The E2M1-grid components and the probe stay on it.)
+  if (!mv.e2m1 && !probe) {
+    if (cdiv(M, 64) * cdiv(N, 64) <= 512) return launch_w4_small<2, 2, 2, 2, 2, 4>(a, stream);
+    if (cdiv(M, 128) * cdiv(N, 128) <= 256) return launch_w4_small<4, 4, 4, 2, 2, 4>(a, stream);
+  }
   constexpr int NS = 4;
   const int tiles_m = (int)cdiv(M, 256), tiles_n = (int)cdiv(N, 256);
   const int total = tiles_m * tiles_n;
