@@ -1371,11 +1371,21 @@ int launch_gemm_w8_mfma_probe(const GemmW8Args& a, hipStream_t stream) {
 
 // Which kernel family serves a shape (the decomposition launch writes the layout it wants).
 enum class W8Path { kDecode, kFillSmall, kFillLarge, kStaged };
+// 64 x 128 tiles with 64 bytes of K per stage: 64 KB of LDS, two workgroups per CU.  They serve outputs of 257 to 512
+// such tiles (measured, us, against one workgroup per CU -- 128 bytes of K per stage or the 128 x 256 tile: 130 x 4096 x
+// 14336 30.9 / 36.8, 777 x 4096 x 4096 37.8 / 42.3, 400 x 8192 x 8192 68.6 / 79.3, 2048 x 1024 x 2048 18.5 / 23.6).  With
+// at most 256 the deeper stage is better (512 x 4096 x 4096 26.4 against 27.2), with more the 128 x 256 tile (1500 x 4096
+// x 4096, 768 tiles, 57.1 against 62.2).
+static bool w8_pairs_of_tiles(int64_t M, int64_t N) {
+  const int64_t t = cdiv(M, 64) * cdiv(N, 128);
+  return M > 32 && t > 256 && t <= 512;
+}
 static W8Path w8_path(int64_t M, int64_t K, int64_t N) {
   const bool wide = cdiv(N, 16) > 512;  // many column tiles
   const bool k64 = K % 64 == 0 && K >= 64;
   if (2 * M <= 32) return W8Path::kDecode;
   if (2 * M <= 64) return (wide && k64) ? W8Path::kFillSmall : W8Path::kDecode;
+  if (k64 && w8_pairs_of_tiles(M, N)) return W8Path::kFillSmall;
   if (cdiv(M, 128) * cdiv(N, 256) < 128) return k64 ? W8Path::kFillSmall : W8Path::kStaged;
   return k64 ? W8Path::kFillLarge : W8Path::kStaged;
 }
@@ -1392,7 +1402,7 @@ int gemm_w8_blocked_bk(int64_t M, int64_t K, int64_t N) {
   if (gemm_w8_is_fused(M, K, N)) return 0;
   const W8Path p = w8_path(M, K, N);
   if (p == W8Path::kFillLarge) return 64;
-  if (p == W8Path::kFillSmall) return K % 128 == 0 ? 128 : 64;
+  if (p == W8Path::kFillSmall) return K % 128 == 0 && !w8_pairs_of_tiles(M, N) ? 128 : 64;
   return 0;
 }
 
@@ -1449,14 +1459,17 @@ int launch_gemm_w8(const GemmW8Args& a, hipStream_t stream) {
     // 128 x 4096 x 4096, 19 vs 22 us at 32 x 4096 x 14336; with more tiles than CUs the larger tiles win again).
     // At most half a chip of those: tiles of 32 channels, four waves (the four K groups of one 32 x 32 tile), two
     // workgroups per CU.
-    if (deep && wgs(32, 64) <= 128)
+    if (w8_pairs_of_tiles(M, N))
+      rc = launch_dma<64, 128, 2, 4, 4>(a, stream);
+    else if (deep && wgs(32, 64) <= 128)
       rc = launch_dma<32, 32, 1, 1, 4, false, false, 128, 4>(a, stream);
     else if (deep && wgs(32, 64) <= 256)
       rc = launch_dma<32, 64, 1, 2, 4, false, false, 128, 4>(a, stream);
     else
     // eight waves measured 30 vs 31.6 us at 128 x 4096 x 14336; as 2 x 2 waves in two K groups (a third fewer
     // fragment reads) 31.4, as sixteen waves (2 x 4 in two K groups) 31.3
-    if (2 * M > 64 && wgs(64, 128) >= 200)
+    // (64 x 64 tiles beyond one workgroup per CU are worse than fewer 64 x 128 ones: 130 x 8192 x 8192 49.6 against 35.5)
+    if (2 * M > 64 && (wgs(64, 128) >= 200 || wgs(64, 64) > 256))
       rc = deep ? launch_dma<64, 128, 2, 4, 4, false, false, 128>(a, stream) : launch_dma<64, 128, 2, 2, 8>(a, stream);
     else if (2 * M > 64 && wgs(64, 64) >= 200)
       rc = deep ? launch_dma<64, 64, 2, 2, 4, false, false, 128>(a, stream) : launch_dma<64, 64, 2, 2, 6>(a, stream);
