@@ -734,6 +734,22 @@ __device__ __forceinline__ void lds_dma16(const int8_t* gbase, uint32_t voff, ui
                : "memory", "m0");
 }
 
+// The same under a lane mask (all lanes or none: the instruction counts as outstanding either way).
+__device__ __forceinline__ void lds_dma16_masked(const int8_t* gbase, uint32_t voff, uint32_t lds_addr, uint64_t mask) {
+  const uint32_t mlo = __builtin_amdgcn_readfirstlane((uint32_t)mask), mhi = __builtin_amdgcn_readfirstlane((uint32_t)(mask >> 32));
+  mask = ((uint64_t)mhi << 32) | mlo;
+  const uint64_t g = reinterpret_cast<uint64_t>(gbase);
+  const uint32_t glo = __builtin_amdgcn_readfirstlane((uint32_t)g), ghi = __builtin_amdgcn_readfirstlane((uint32_t)(g >> 32));
+  gbase = reinterpret_cast<const int8_t*>(((uint64_t)ghi << 32) | glo);
+  lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+  uint64_t saved;
+  asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, %0"
+               : "=&s"(saved)
+               : "v"(voff), "s"(gbase), "s"(lds_addr), "s"(mask)
+               : "memory", "m0");
+}
+
 // Moves one accumulator register to a vector register at this point of the program.  Left to the
 // register allocator, an epilogue over 256 accumulators copies all of them out up front, spills, and
 // every reload of a spilled value then waits for the stores issued before it.
@@ -784,10 +800,11 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (2 * BMH * BN <= 128 * 256 && WM
   constexpr int HS = BK / 32 / KS;  // MFMA K extents (32 bytes) per stage and wave
   constexpr int CPR = BK / 16;      // 16-byte chunks per row
   constexpr int RPI = 1024 / BK;    // rows per fill instruction
-  constexpr int L = R / (RPI * NW);  // fill instructions per wave and stage
+  constexpr int NB = R / RPI;        // fill instructions per stage ...
+  constexpr int L = (NB + NW - 1) / NW;  // ... and per wave (the last one of a wave may be a blank)
   constexpr int STAGE = R * BK;
   static_assert(BK == 64 || BK == 128, "stage depth");
-  static_assert(R % (RPI * NW) == 0 && TMH % 32 == 0 && TN % 32 == 0 && BMH % RPI == 0, "tile shape");
+  static_assert(R % RPI == 0 && TMH % 32 == 0 && TN % 32 == 0 && BMH % RPI == 0, "tile shape");
   static_assert(NS >= 3 && (NS - 2) * L < 64, "stage count");
   static_assert((BK / 32) % KS == 0 && (KS == 1 || (!BF16 && !PROBE && 16 % KS == 0)), "K groups");
   extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -826,14 +843,15 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (2 * BMH * BN <= 128 * 256 && WM
   int64_t kadv[L];  // bytes between consecutive stages of this instruction's source
 #pragma unroll
   for (int q = 0; q < L; ++q) {
-    const int blk = q * NW + wave;
+    const int blk = min(q * NW + wave, NB - 1);
     const int lc = pc ^ swz(blk * RPI + rr);  // logical chunk this lane fetches
     kadv[q] = BK;
     if (blk < ROWS_A / RPI) {
       const int comp = blk / (BMH / RPI);
       if (blocked) {
         voff[q] = (uint32_t)(lane * 16);
-        gbase[q] = (comp ? a.q2 : a.q1) + (m0 / RPI + blk % (BMH / RPI)) * 1024;
+        // (a tile of 96 rows may reach past the padded rows)
+        gbase[q] = (comp ? a.q2 : a.q1) + min(m0 / RPI + blk % (BMH / RPI), a.a_step / 1024 - 1) * 1024;
         kadv[q] = a.a_step;
       } else {
         const int64_t mrow = min(m0 + (BF16 ? comp * BMH : 0) + (blk % (BMH / RPI)) * RPI + rr, M - 1);
@@ -869,8 +887,15 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (2 * BMH * BN <= 128 * 256 && WM
     gbase[q] = reinterpret_cast<const int8_t*>(uniform64(reinterpret_cast<uint64_t>(gbase[q])));
     kadv[q] = (int64_t)uniform64((uint64_t)kadv[q]);
   }
+  [[maybe_unused]] const uint64_t last_fill = wave < NB - (L - 1) * NW ? ~0ull : 0ull;
   auto issue_one = [&](int kt, int q) {  // q is a compile-time constant at every call site
-    lds_dma16(gbase[q], voff[q], ldst[q] + (uint32_t)((kt % NS) * STAGE));
+    const uint32_t dst = ldst[q] + (uint32_t)((kt % NS) * STAGE);
+    if constexpr (NB % NW != 0) {
+      if (q == L - 1) lds_dma16_masked(gbase[q], voff[q], dst, last_fill);
+      else lds_dma16(gbase[q], voff[q], dst);
+    } else {
+      lds_dma16(gbase[q], voff[q], dst);
+    }
     gbase[q] += kadv[q];
   };
   auto issue = [&](int kt) {
@@ -1482,7 +1507,15 @@ int launch_gemm_w8(const GemmW8Args& a, hipStream_t stream) {
     // a SIMD always has another wave to issue from while one waits.  Three or five stages, half-size tiles (two
     // workgroups per CU) and 128 bytes of K per barrier on 64x256 or 128x128 tiles (a 256x256 tile of 128-byte
     // stages does not fit LDS three deep) measured no better.
-    rc = launch_dma<128, 256, 4, 4, 4>(a, stream);
+    // Tiles of 96 rows (twelve waves, the same 64 x 64 wave tiles) where they need no more rounds of one tile per CU: a
+    // round takes 0.87 of the time.  us at 128 / 96 rows: 777 x 4096 x 14336 (392 / 504 tiles) 119 / 106, 576 x 4096 x
+    // 14336 (280 / 336) 105 / 88, 672 x 8192 x 8192 (192 / 224) 105 / 91, 1056 x 8192 x 8192 (288 / 352) 196 / 163; with a
+    // round more, 960 x 4096 x 14336 (448 / 560) 119 / 136.  Five stages measured 3-6 % slower than four.
+    const auto rounds = [&](int bmh) { return cdiv(cdiv(M, bmh) * cdiv(N, 256), 256); };
+    if (rounds(96) <= rounds(128))
+      rc = launch_dma<96, 256, 3, 4, 4>(a, stream);
+    else
+      rc = launch_dma<128, 256, 4, 4, 4>(a, stream);
   } else if (cdiv(M, 128) * cdiv(N, 256) < 128) {
     rc = launch_mfma32<64, 64, 2, 2>(a, stream);
   } else {

@@ -46,7 +46,7 @@ def test_w4(msd, M, K, N):
 
 
 @pytest.mark.parametrize("M,K,N", [(65, 128, 16500), (129, 64, 12000), (129, 192, 8192), (200, 256, 11000), (777, 128, 4100),
-                                   (1024, 64, 4096), (1025, 192, 3900), (2048, 128, 2048), (2049, 64, 2049)])
+                                   (1024, 64, 4096), (1025, 192, 3900), (672, 64, 8192), (193, 192, 28700), (1151, 64, 8100), (2048, 128, 2048), (2049, 64, 2049)])
 def test_w8(msd, M, K, N):
     seed = synth.seed_for(1, M + 7 * N)
     x = synth.activations(seed, M, K, outliers=False)
