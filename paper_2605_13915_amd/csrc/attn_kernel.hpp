@@ -212,6 +212,9 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_kernel(AttnParams
     const bool coded = top > 1e-30f;  // below that every code of the tile is zero (and 127 / top would overflow)
     const float to_code = coded ? __fdiv_rn(127.0f, top) : 0.f;
     const float from_code = coded ? top * (1.0f / 127.0f) : 0.f;
+    float svc[4];  // value scale in units of alpha_P
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt) svc[tt] = sv[tt] * to_code;
     uint32_t vb[8][4];  // filled by the first fragment of the tile
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -283,16 +286,28 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_kernel(AttnParams
           w1 = __builtin_amdgcn_perm(m1[1], m1[0], 0x06040200u);
           w2 = __builtin_amdgcn_perm(m2[1], m2[0], 0x06040200u);
         } else {
+        uint32_t c1[4], c2[4];
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
           const float pr = __builtin_amdgcn_exp2f(s[tt] - m_new);
           lsum += pr;
-          const float t = pr * sv[tt] * to_code;  // P (times s_V) in units of alpha_P
-          const float c1 = fminf(rintf(t), 127.f);
-          const float c2 = fminf(fmaxf(rintf((t - c1) * 254.0f), -127.f), 127.f);
-          w1 |= ((uint32_t)(int)c1 & 0xFFu) << (8 * tt);
-          w2 |= ((uint32_t)(int)c2 & 0xFFu) << (8 * tt);
+          // P (times s_V) in units of alpha_P, v in [0, 127], as v = c1 + c2 / 254: adding 1.5 * 2^23 rounds to the
+          // nearest integer (ties to even) and leaves the code in the low byte; the rest v - c1 is exact and 254 times
+          // it is rounded once.  |c1| and |c2| are at most 127: nothing to clamp.  (Half the instructions of rounding,
+          // clamping and converting: 32 x 8 x 3000 tokens with 12 heads each 51.9 -> 50.2 us, where the vector ALU is the
+          // bound; 5 x 8 x 1079 9.8 -> 9.1.)
+          constexpr float kMagic = 12582912.0f;
+          const float v = pr * svc[tt];
+          const float a = v + kMagic;
+          c1[tt] = __float_as_uint(a);
+          c2[tt] = __float_as_uint(__builtin_fmaf(v - (a - kMagic), 254.0f, kMagic));
         }
+        auto low_bytes = [](const uint32_t (&c)[4]) {
+          return __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[3], c[2], 0x0c0c0400u), __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0400u),
+                                       0x05040100u);
+        };
+        w1 = low_bytes(c1);
+        w2 = low_bytes(c2);
         }
         l_run[f][hh] = l_run[f][hh] * corr[hh] + lsum;
         pk1[hh] = w1;
