@@ -552,7 +552,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mla_kernel(MlaParams p) {
     // that the MFMAs and LDS reads of the one run under the vector instructions of the other (the two waves of a
     // SIMD pass the barrier together and would otherwise be in the same phase all the time).  After the barrier of
     // a step tile it + 1 is visible and nobody reads tile it - 1 any more, whose buffer takes tile it + 2 from the
-    // registers while the loads of tile it + 3 are in flight.  What bounds it: the issue of about 450 vector and 70
+    // registers while the loads of tile it + 3 are in flight.  What bounds it: the issue of about 560 vector and 70
     // matrix instructions per wave and tile, two waves per SIMD (5.9 kcycles per tile of 64 heads; before, with the
     // phases in turn, 9.3).  32 x 4096 tokens, 128 heads 81.3 -> 76.5 us (floor by its 73 G operations 24); 32 heads
     // 44.3 -> 38.3.  Filling LDS without registers (global_load_lds) measured 79.3, wave priorities that keep the two
